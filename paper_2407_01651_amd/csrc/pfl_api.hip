@@ -196,6 +196,9 @@ int pfl_create(pfl_ctx** out, const pfl_params* p, const pfl_buffers* bufs, void
   if (he != hipSuccess) return hip_fail(he, "hipGetDevice");
   he = resolve_reduce_scratch(dev);
   if (he != hipSuccess) return hip_fail(he, "hipGetSymbolAddress(reduction scratch)");
+  int cus = 0;
+  he = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (he != hipSuccess || cus <= 0) return hip_fail(he, "hipDeviceGetAttribute(compute units)");
   pfl_ctx* c = new pfl_ctx();
   c->device = dev;
   c->p = *p;
@@ -276,14 +279,15 @@ int pfl_create(pfl_ctx** out, const pfl_params* p, const pfl_buffers* bufs, void
     const size_t lim = (size_t)1 << 32;
     d.fast = (L.pops_bytes < lim && L.hist_bytes < lim) ? 1 : 0;
     d.plane32 = ((size_t)L.N * 8 < lim) ? 1 : 0;
-    // 3D: z planes per workgroup (the march's prologue of two planes against
-    // enough workgroups to fill the chip; 256^3, all storage types: 128 planes
-    // 2-4% faster than 32, 16 slower); PFL_ZCHUNK overrides it for tuning
-    d.zc = p->nz < 128 ? p->nz : 128;
+    // 3D: z planes per workgroup; 0 leaves the choice to the launch, which
+    // knows how many workgroups the kernel runs at once; PFL_ZCHUNK sets it
+    // for tuning
+    d.zc = 0;
     if (const char* zs = std::getenv("PFL_ZCHUNK")) {
       const int v = std::atoi(zs);
       if (v > 0) d.zc = v < p->nz ? v : p->nz;
     }
+    d.cus = cus;
     d.sr = ((p->store == PFL_F16 || p->store == PFL_BF16) && p->rounding == PFL_ROUND_STOCHASTIC) ? 1 : 0;
     // Automatic write policy: stream the stores past the 256 MiB last-level
     // cache when the populations and history read plus written per step do
