@@ -35,8 +35,8 @@ CSRC = "paper_2407_01651_amd/csrc/"
 # sources whose hash they were taken on
 PROFILES = {
     3: ("profiles/step3d_coupled3d_256.md",
-        (CSRC + "pfl_step3d.hip", CSRC + "pfl_step3d_lowp.hip", CSRC + "pfl_step3d_impl.h",
-         CSRC + "pfl_util.h", CSRC + "pfl_dev.h", "paper_2407_01651_amd/build.py")),
+        (CSRC + "pfl_step3d.hip", CSRC + "pfl_step3d_lowp.hip", CSRC + "pfl_step3d.h",
+         CSRC + "pfl_step3d_f64.h", CSRC + "pfl_step3d_impl.h", CSRC + "pfl_util.h", CSRC + "pfl_dev.h", "paper_2407_01651_amd/build.py")),
     2: ("profiles/step2d_coupled2d_2048.md",
         (CSRC + "pfl_step2d.hip", CSRC + "pfl_step2d_lowp.hip", CSRC + "pfl_step2d_impl.h",
          CSRC + "pfl_step2d.h", CSRC + "pfl_util.h", CSRC + "pfl_dev.h", "paper_2407_01651_amd/build.py")),

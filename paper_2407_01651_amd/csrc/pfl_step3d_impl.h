@@ -1,5 +1,6 @@
-// Fused 3D time step: D3Q19 flow, D3Q7 bubble phase, order parameter, solute
-// and heat, advanced by one step in one launch.  The scheme is the 2D step's
+// Fused 3D time step in FP32 compute (FP32, FP16 and BF16 storage): D3Q19 flow,
+// D3Q7 bubble phase, order parameter, solute and heat, advanced by one step in
+// one launch.  The scheme is the 2D step's
 // with the 3D lattices: isotropic D3Q19 stencils (Appendix B), the cubic
 // anisotropy with the crystal rotated about z (Sec. 3.3), the D3Q19 MRT
 // collision relaxing the five traceless stress moments, D3Q7 collisions
@@ -25,119 +26,11 @@
 // addressed from a 64-bit plane base plus a 32-bit in-plane byte offset, so
 // population buffers beyond 4 GiB (256^3 in FP64) keep the cheap addressing.
 #pragma once
-#include "pfl_kernels.h"
-#include "pfl_util.h"
+#include "pfl_step3d.h"
 
 namespace pfl {
 
 namespace {
-
-// Column tile: 32 x 8 nodes, 256 threads (rows of 32 nodes keep each wave's
-// loads and stores in whole or half 128-byte lines).  FP64 runs one wave per
-// SIMD either way; against 32 x 4 the taller column spreads the ring pulls
-// over more nodes (coupled 256^3 FP64 2.65k -> 2.75k MLUPS) and fits the
-// LDS (55 KB).
-template <class CT>
-struct Col3 {
-  static constexpr int TX = 32, TY = sizeof(CT) == 8 ? 8 : 16;
-  static constexpr int NT = TX * TY;
-};
-
-// One LDS plane of the tile plus R rings in x and y.
-template <class CT, int R>
-struct Pl {
-  static constexpr int X = Col3<CT>::TX + 2 * R, Y = Col3<CT>::TY + 2 * R;
-  static constexpr int N = X * Y;
-  __device__ static constexpr int at(int y, int x) { return y * X + x; }
-};
-
-// Ring slot of plane p among n slots.
-__device__ __forceinline__ int ring_slot(int p, int n) {
-  const int s = p % n;
-  return s < 0 ? s + n : s;
-}
-
-// Pull the stored values of one set at node (x, y, z), general addressing:
-// periodic wrap, half-way bounce-back at a wall or specular reflection at a
-// symmetry plane on each axis, from per-axis source offsets computed once
-// per node.
-template <int Q, class ST, class CT, bool SYM>
-__device__ __forceinline__ void pull3_general(const typename Store<ST>::raw* __restrict__ base,
-                                              const DevParams& P, int x, int y, int z, CT f[Q]) {
-  using L = Lat<Q>;
-  AxisSrc ax, ay, az;
-  axis_src(x, P.nx, P.wall[0], SYM && sym_side(P, 0, true), SYM && sym_side(P, 0, false), 1, ax);
-  axis_src(y, P.ny, P.wall[1], SYM && sym_side(P, 1, true), SYM && sym_side(P, 1, false), P.nx, ay);
-  axis_src(z, P.nz, P.wall[2], SYM && sym_side(P, 2, true), SYM && sym_side(P, 2, false), P.nx * P.ny, az);
-  const int m = SYM ? sym_touch(P, x, y, z) : 0;
-  const long long own = ((long long)z * P.ny + y) * P.nx + x;
-  const long long N = P.N;
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const int cx = L::c[i][0] + 1, cy = L::c[i][1] + 1, cz = L::c[i][2] + 1;
-    const bool b = ax.wall[cx] || ay.wall[cy] || az.wall[cz];
-    const int j = SYM ? pulled_population<Q>(i, m) : i;
-    const long long e = b ? (long long)L::opp[i] * N + own
-                          : (long long)j * N + (own + ax.off[cx] + ay.off[cy] + az.off[cz]);
-    f[i] = Store<ST>::template ld<CT>(base + e);
-  }
-}
-
-// Pull at a node whose sources x - c_i all lie inside the domain: a 64-bit
-// plane base per population and one 32-bit in-plane byte offset (the source
-// node's offset is non-negative and below N S < 2^32).
-template <int Q, class ST, class CT>
-__device__ __forceinline__ void pull3_fast(const typename Store<ST>::raw* __restrict__ base,
-                                           const DevParams& P, uint32_t nbyte, CT f[Q]) {
-  using L = Lat<Q>;
-  constexpr uint32_t S = sizeof(typename Store<ST>::raw);
-  const uint32_t sxy = (uint32_t)P.nx * (uint32_t)P.ny;
-#pragma unroll
-  for (int i = 0; i < Q; ++i) {
-    const uint32_t shift = ((uint32_t)L::c[i][0] + (uint32_t)L::c[i][1] * (uint32_t)P.nx +
-                            (uint32_t)L::c[i][2] * sxy) * S;
-    f[i] = Store<ST>::template ld<CT>(at_byte<ST>(base + (size_t)i * (size_t)P.N, nbyte - shift));
-  }
-}
-
-template <int Q, class ST, class CT, bool SYM>
-__device__ __forceinline__ void pull3(bool fast, const typename Store<ST>::raw* __restrict__ base,
-                                      const DevParams& P, int x, int y, int z, CT f[Q]) {
-  if (fast) {
-    const uint32_t nbyte = (uint32_t)((z * P.ny + y) * P.nx + x) * (uint32_t)sizeof(typename Store<ST>::raw);
-    pull3_fast<Q, ST, CT>(base, P, nbyte, f);
-  } else {
-    pull3_general<Q, ST, CT, SYM>(base, P, x, y, z, f);
-  }
-}
-
-// Isotropic D3Q19 gradient (1/cs2) sum_i w_i c_i f(x + c_i) and Laplacian
-// (2/cs2) sum_i w_i [f(x + c_i) - f(x)] from three LDS planes (below, at,
-// above the node), (y, x) in the plane geometry PL.
-template <class CT, class PL>
-__device__ __forceinline__ void grad19p(const CT* const pl[3], int y, int x, CT g[3]) {
-  using L = Lat<19>;
-  CT a0 = CT(0), a1 = CT(0), a2 = CT(0);
-#pragma unroll
-  for (int i = 1; i < 19; ++i) {
-    const CT v = CT(L::w[i]) * pl[L::c[i][2] + 1][PL::at(y + L::c[i][1], x + L::c[i][0])];
-    if (L::c[i][0]) a0 += CT(L::c[i][0]) * v;
-    if (L::c[i][1]) a1 += CT(L::c[i][1]) * v;
-    if (L::c[i][2]) a2 += CT(L::c[i][2]) * v;
-  }
-  g[0] = CT(3) * a0;
-  g[1] = CT(3) * a1;
-  g[2] = CT(3) * a2;
-}
-template <class CT, class PL>
-__device__ __forceinline__ CT lap19p(const CT* const pl[3], int y, int x) {
-  using L = Lat<19>;
-  const CT c = pl[1][PL::at(y, x)];
-  CT a = CT(0);
-#pragma unroll
-  for (int i = 1; i < 19; ++i) a += CT(L::w[i]) * (pl[L::c[i][2] + 1][PL::at(y + L::c[i][1], x + L::c[i][0])] - c);
-  return CT(6) * a;
-}
 
 template <class CT>
 struct FlowNode3 {
@@ -252,38 +145,23 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
   const raw* fin_c = fin + (size_t)(CC ? P.o_c : 0) * (size_t)N;
   const raw* fin_th = fin + (size_t)(TH ? P.o_th : 0) * (size_t)N;
   const CT k1 = K.k1;
-  constexpr bool DEV = !std::is_same<ST, double>::value;
-  const CT r_phi = DEV ? CT(1) : CT(0), r_psi = DEV ? CT(-1) : CT(0);
-  const CT r_C = DEV ? K.C_ref : CT(0), r_H = DEV ? K.theta0 : CT(0);
+  // moments are the rest value plus the sum of the stored deviations
+  const CT r_phi = CT(1), r_psi = CT(-1);
+  const CT r_C = K.C_ref, r_H = K.theta0;
   const bool first = P.first != 0;
 
-  // FP64 and FP32 storage with flow and bubble phase: a thread keeps the
-  // flow, psi and C populations it pulls for its own node in phase A, for the
-  // plane's phase C one step later (two planes in registers), so that phase C
-  // pulls only phi and theta.  The FP64 kernel runs one wave per SIMD with
-  // room to spare, the FP32 one still fits two (256^3 FP64 2.55k -> 2.65k,
-  // FP32 6.03k -> 6.42k MLUPS); with 16-bit storage the kept values spill
-  // (FP16 6.34k -> 6.18k), and the other field combinations would lose a
-  // wave per SIMD.
-  constexpr bool KEEP = FLOWX && sizeof(raw) >= 4;
-  // FP64 storage (one wave per SIMD, registers to spare) also keeps the own
-  // node's phi populations; phase A pulls phi two planes ahead, so three
-  // planes are held: kph0 for this step's phase C (plane t), kph1 (t + 1),
-  // kph2 (t + 2, pulled in this step's phase A)
-  constexpr bool KEEPPHI = KEEP && PHI && sizeof(raw) == 8;
-  constexpr int KP = KEEPPHI ? QP : 1;
-  CT kph0[KP], kph1[KP], kph2[KP];
-  auto rot_phi = [&]() {
-    if constexpr (KEEPPHI) {
-#pragma unroll
-      for (int i = 0; i < KP; ++i) { kph0[i] = kph1[i]; kph1[i] = kph2[i]; }
-    }
-  };
+  // FP32 storage with flow and bubble phase: a thread keeps the flow, psi and C
+  // populations it pulled for its own node in phase A, for the plane's phase C
+  // one step later (two planes in registers), so that phase C pulls only phi
+  // and theta.  The kernel still fits two waves per SIMD (256^3 6.03k -> 6.42k
+  // MLUPS); with 16-bit storage the kept values spill (FP16 6.34k -> 6.18k), and
+  // the other field combinations would lose a wave per SIMD.
+  constexpr bool KEEP = FLOWX && sizeof(raw) == 4;
   // ---- phase A: phi of plane p on the tile and R rings
   auto load_phi = [&](int p) {
     const bool fast = fast_at(p);
     CT* dst = s_phi + ring_slot(p, NPH) * PR::N;
-    auto one = [&](int k, bool keep) {
+    auto one = [&](int k) {
       const int tx = k % PR::X - R, ty = k / PR::X - R;
       int gx = bx0 + tx, gy = by0 + ty, gz = p;
       if (!fast) {
@@ -299,50 +177,19 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
 #pragma unroll
         for (int i = 0; i < QP; ++i) d += f[i];
         hphi = r_phi + d;
-        if constexpr (KEEPPHI) {
-          if (keep) {
-#pragma unroll
-            for (int i = 0; i < QP; ++i) kph2[i] = f[i];
-          }
-        }
       }
       dst[k] = hphi;
     };
-    if constexpr (KEEPPHI) {
-      // the own interior position first, then the ring positions (the R top
-      // rows, the R bottom rows, then the side columns), those on the last
-      // threads as below
-      constexpr int NPASS = 1 + (PR::N - NT + NT - 1) / NT;
-#pragma unroll 1
-      for (int it = 0; it < NPASS; ++it) {
-        int k;
-        if (it == 0) {
-          k = PR::at(ly + R, lx + R);
-        } else {
-          const int r = (it - 1) * NT + (NT - 1 - tid);
-          if (r >= PR::N - NT) continue;
-          if (r < R * PR::X) {
-            k = r;
-          } else if (r < 2 * R * PR::X) {
-            k = (PR::Y - R) * PR::X + (r - R * PR::X);
-          } else {
-            const int q = r - 2 * R * PR::X, c = q % (2 * R);
-            k = (R + q / (2 * R)) * PR::X + (c < R ? c : PR::X - 2 * R + c);
-          }
-        }
-        one(k, it == 0);
-      }
-    } else if constexpr (KEEP) {
+    if constexpr (KEEP) {
       // positions beyond the first NT go to the last threads (the first ones
       // take the extra ring positions of load_rest), so no wave does both
-      // (A/B on one box: 256^3 FP64 2.82k -> 2.88k, FP32 7.31k -> 7.39k
-      // MLUPS; the kernels without kept populations measured slower with
-      // this loop and keep the plain one)
+      // (A/B on one box: 256^3 FP32 7.31k -> 7.39k MLUPS; the kernels without
+      // kept populations measured slower with this loop and keep the plain one)
       constexpr int NPASS = (PR::N + NT - 1) / NT;
 #pragma unroll 1
       for (int it = 0; it < NPASS; ++it) {
         const int k = it == 0 ? tid : it * NT + (NT - 1 - tid);
-        if (k < PR::N) one(k, false);
+        if (k < PR::N) one(k);
       }
     } else {
       for (int k = tid; k < PR::N; k += NT) {
@@ -562,9 +409,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
   // phi planes z0 - 2, z0 - 1 before the march when phi runs two planes ahead
   if constexpr (FLOWX) {
     load_phi(z0 - 2);
-    rot_phi();
     load_phi(z0 - 1);
-    rot_phi();
   }
   for (int t = z0 - 2; t < z1; ++t) {
     load_phi(t + (FLOWX ? 2 : 1));
@@ -644,12 +489,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
           }
         }
         if constexpr (PHI) {
-          if constexpr (KEEPPHI) {
-#pragma unroll
-            for (int i = 0; i < QP; ++i) fph[i] = kph0[i];
-          } else {
-            pull3<QP, ST, CT, SYM>(fast, fin_phi, P, x, y, z, fph);
-          }
+          pull3<QP, ST, CT, SYM>(fast, fin_phi, P, x, y, z, fph);
 #pragma unroll
           for (int i = 0; i < QP; ++i) dphi += fph[i];
           phi = r_phi + dphi;
@@ -947,8 +787,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
               const CT cx = CT(LP::c[i][0]), cy = CT(LP::c[i][1]), cz = CT(LP::c[i][2]);
               const CT w = CT(LP::w[i]);
               const CT cv = cx * v[0] + cy * v[1] + cz * v[2];
-              if constexpr (DEV) feq[i] = w * dphi + w * phi * cv * CT(1.0 / LP::cs2);
-              else feq[i] = w * phi * (CT(1) + cv * CT(1.0 / LP::cs2));
+              feq[i] = w * dphi + w * phi * cv * CT(1.0 / LP::cs2);
               G[i] = w * (cx * fl[0] + cy * fl[1] + cz * fl[2]) * CT(1.0 / LP::cs2);
               const CT d = fph[i] - feq[i];
               jf[0] += cx * d; jf[1] += cy * d; jf[2] += cz * d;
@@ -1064,8 +903,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
               // H (the sum of g) is rho times the model's H: the rest equilibrium
               // rho H + (w - 1) theta less w theta0 is dH + (w - 1) dtheta
               if (i == 0) {
-                if constexpr (DEV) geq = K.varheat ? dH + (w - CT(1)) * dtheta : -h + w * dtheta;
-                else geq = H + (w - CT(1)) * theta;
+                geq = K.varheat ? dH + (w - CT(1)) * dtheta : -h + w * dtheta;
               }
               const CT G = w * (cx * dHv[0] + cy * dHv[1] + cz * dHv[2]) * CT(1.0 / LS::cs2);
               CT gs = geq + (CT(1) - s1) * (cx * jf[0] + cy * jf[1] + cz * jf[2]) * CT(0.5) + (CT(1) - CT(0.5) * s1) * G;
@@ -1100,36 +938,10 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
 #pragma unroll
       for (int w = 0; w < KW; ++w) kA16[w] = kB16[w];
     }
-    rot_phi();
     // no barrier here: the next phase A writes slots this phase C does not
     // read (the slot counts above), the D_phi/v0 plane is read before the
     // barrier after phase B, and the momentum plane only in phase B
   }
-}
-
-// z planes per workgroup of a launch whose columns number cols and of which
-// slots workgroups run at once.  A chunk of zc planes costs its zc iterations
-// and two more that only fill the rings, so a launch of r full rounds costs
-// r (zc + 2) with the chunk that makes the rounds full, zc = ceil(nz / (r
-// slots / cols)).  The smallest cost wins; within 1% the shorter chunk does
-// (256^3 FP64: 128 planes in two rounds against 256 in one, 3.06k against
-// 3.02k MLUPS).  Measured, one chunk length of 128 planes before, against this
-// rule: 96^3 FP64 psi + C + theta 1055 -> 138 us a step (14 chunks of 7),
-// 90 x 70 x 50 FP32 650 -> 71 us (17 of 3), 160^3 FP16 coupled 2023 -> 597 us
-// (5 of 32); between its minima the step time follows the cost within 10%.
-inline int chunk_planes(long long cols, int nz, long long slots) {
-  const long long r0 = (cols + slots - 1) / slots;
-  int best = nz;
-  double cost = 0.0;
-  for (long long r = r0; r < r0 + 16; ++r) {
-    const long long n = r * slots / cols;             // chunks per column, at least 1
-    const int zc = (int)((nz + n - 1) / n);
-    const double c = (double)r * (zc + 2);
-    if (r == r0 || c < cost) cost = c;
-    if (c <= 1.01 * cost) best = zc;
-    if (zc == 1) break;
-  }
-  return best;
 }
 
 template <int FIELDS, class ST, class HT, class CT, bool SYM, bool STREAM>
@@ -1138,12 +950,7 @@ hipError_t launch_step3d_k(const DevParams& Pc, const void* fin, void* fout, voi
   using T = Col3<CT>;
   using raw = typename Store<ST>::raw;
   const auto kernel = step3d_kernel<FIELDS, ST, HT, CT, SYM, STREAM>;
-  // workgroups that fit a CU, a property of the compiled kernel
-  static const int per_cu = [&] {
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, T::NT, 0);
-    return e == hipSuccess && n > 0 ? n : 1;
-  }();
+  static const int per_cu = blocks_per_cu(kernel, T::NT);
   DevParams P = Pc;
   const long long cols = (long long)((P.nx + T::TX - 1) / T::TX) * ((P.ny + T::TY - 1) / T::TY);
   if (P.zc <= 0) P.zc = chunk_planes(cols, P.nz, (long long)P.cus * per_cu);
