@@ -1,6 +1,7 @@
 // Initialisation, node-form state export/import and FP64 reductions, for
 // 2D and 3D lattices.  None of these is on the per-step path.
 #include "pfl_kernels.h"
+#include "pfl_util.h"
 
 #include <mutex>
 
@@ -198,23 +199,54 @@ __global__ __launch_bounds__(BT) void state_kernel(const DevParams P, int fields
   }
 }
 
+// Threads of a reduction block: with RED_BLOCKS blocks the chip holds RBT / 256
+// waves per SIMD or fewer, and the kernel, which reads every stored value once, is
+// bound by how many loads are in flight (a reduction of 200 x 160 x 120 FP32 coupled,
+// with its read-back: 574 us with 256 threads and a division chain per population;
+// with per-axis sources 369 us with 256, 241 with 512, 247 with 1024).
+constexpr int RBT = 512;
+
+// Node-form populations of one set at a node from its axis sources (those of the
+// step's pulls): m the symmetry planes it touches.
+template <int Q, class ST>
+__device__ __forceinline__ void gather_at(const DevParams& P, const typename Store<ST>::raw* base, const double* ref,
+                                          long long own, const AxisSrc (&a)[3], int m, double f[Q]) {
+  using L = Lat<Q>;
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    const int cx = L::c[i][0] + 1, cy = L::c[i][1] + 1, cz = L::c[i][2] + 1;
+    const bool b = a[0].wall[cx] || a[1].wall[cy] || a[2].wall[cz];
+    const int j = m ? pulled_population<Q>(i, m) : i;
+    const long long e = b ? (long long)L::opp[i] * P.N + own
+                          : (long long)j * P.N + (own + a[0].off[cx] + a[1].off[cy] + a[2].off[cz]);
+    f[i] = Store<ST>::template ld<double>(base + e) + ref[i];
+  }
+}
+
 template <int QN, int QP, int QS, class ST, class HT>
-__global__ __launch_bounds__(BT) void reduce_kernel(const DevParams P, int fields,
-                                                    const typename Store<ST>::raw* __restrict__ pops,
-                                                    const HT* __restrict__ hist, int hist_planes,
-                                                    double* __restrict__ red) {
+__global__ __launch_bounds__(RBT) void reduce_kernel(const DevParams P, int fields,
+                                                     const typename Store<ST>::raw* __restrict__ pops,
+                                                     const HT* __restrict__ hist, int hist_planes,
+                                                     double* __restrict__ red) {
   double acc[RED_VALS] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (long long n = (long long)blockIdx.x * BT + threadIdx.x; n < P.N; n += (long long)gridDim.x * BT) {
-    const int x = (int)(n % P.nx);
-    const int y = (int)((n / P.nx) % P.ny);
-    const int z = (int)(n / ((long long)P.nx * P.ny));
+  // at most 2^31 nodes: 32-bit coordinates
+  const uint32_t nx = (uint32_t)P.nx, ny = (uint32_t)P.ny;
+  for (long long n = (long long)blockIdx.x * RBT + threadIdx.x; n < P.N; n += (long long)gridDim.x * RBT) {
+    const uint32_t row = (uint32_t)n / nx;
+    const int x = (int)((uint32_t)n - row * nx), z = (int)(row / ny), y = (int)(row - (uint32_t)z * ny);
+    AxisSrc a[3];
+    axis_src(x, P.nx, P.wall[0], sym_side(P, 0, true), sym_side(P, 0, false), 1, a[0]);
+    axis_src(y, P.ny, P.wall[1], sym_side(P, 1, true), sym_side(P, 1, false), P.nx, a[1]);
+    axis_src(z, P.nz, P.wall[2], sym_side(P, 2, true), sym_side(P, 2, false), P.nx * P.ny, a[2]);
+    const int m = sym_touch(P, x, y, z);
     bool bad = false;
     double phi = 1.0, psi = -1.0, C = 0.0;
     auto zeroth = [&](auto qtag, int off, const double* ref) {
       constexpr int Q = decltype(qtag)::value;
       double f[Q];
-      gather_set<Q, ST>(P, pops + (long long)off * P.N, ref, x, y, z, f);
+      gather_at<Q, ST>(P, pops + (long long)off * P.N, ref, n, a, m, f);
       double s = 0.0;
+#pragma unroll
       for (int i = 0; i < Q; ++i) { s += f[i]; bad = bad || !isfinite(f[i]); }
       return s;
     };
@@ -223,6 +255,7 @@ __global__ __launch_bounds__(BT) void reduce_kernel(const DevParams P, int field
     if (fields & F_PSI) psi = zeroth(std::integral_constant<int, QS>{}, P.o_psi, P.ref_psi);
     if (fields & F_C) C = zeroth(std::integral_constant<int, QS>{}, P.o_c, P.ref_c);
     if (fields & F_TH) zeroth(std::integral_constant<int, QS>{}, P.o_th, P.ref_th);
+#pragma unroll 4
     for (int hp = 0; hp < hist_planes; ++hp) bad = bad || !isfinite((double)hist[(long long)hp * P.N + n]);
     const double gas = 1.0 - phi;
     acc[0] += phi;
@@ -235,7 +268,7 @@ __global__ __launch_bounds__(BT) void reduce_kernel(const DevParams P, int field
     acc[7] += bad ? 1.0 : 0.0;
   }
   // wave64 shuffle, then across the block's waves in LDS (fixed order)
-  __shared__ double s_acc[BT / 64][RED_VALS];
+  __shared__ double s_acc[RBT / 64][RED_VALS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int v = 0; v < RED_VALS; ++v) {
@@ -246,19 +279,31 @@ __global__ __launch_bounds__(BT) void reduce_kernel(const DevParams P, int field
   __syncthreads();
   if (threadIdx.x < RED_VALS) {
     double a = 0.0;
-    for (int w = 0; w < BT / 64; ++w) a += s_acc[w][threadIdx.x];
+    for (int w = 0; w < RBT / 64; ++w) a += s_acc[w][threadIdx.x];
     red[(long long)blockIdx.x * RED_VALS + threadIdx.x] = a;
   }
 }
 
-__global__ void reduce_final(double* red) {
-  // one wave; lane v < RED_VALS sums the per-block partials in block order
-  const int v = threadIdx.x;
-  if (v >= RED_VALS) return;
+__global__ __launch_bounds__(1024) void reduce_final(double* red) {
+  // thread t sums value t % RED_VALS of every 128th block's partials, the
+  // wave's eighths by shuffles and the waves in LDS: a fixed order (one lane
+  // per value took 13 us over the 512 blocks, this 3)
+  const int v = threadIdx.x % RED_VALS;
   double a = 0.0;
-  for (int b = 0; b < RED_BLOCKS; ++b) a += red[(long long)b * RED_VALS + v];
-  red[(long long)RED_BLOCKS * RED_VALS + v] = a;
+#pragma unroll
+  for (int b = threadIdx.x / RED_VALS; b < RED_BLOCKS; b += 1024 / RED_VALS) a += red[(long long)b * RED_VALS + v];
+  for (int off = 32; off >= RED_VALS; off >>= 1) a += __shfl_down(a, off, 64);
+  __shared__ double s[16][RED_VALS];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane < RED_VALS) s[wave][lane] = a;
+  __syncthreads();
+  if (threadIdx.x < RED_VALS) {
+    double t = 0.0;
+    for (int w = 0; w < 16; ++w) t += s[w][threadIdx.x];
+    red[(long long)RED_BLOCKS * RED_VALS + threadIdx.x] = t;
+  }
 }
+static_assert(64 % RED_VALS == 0 && RED_BLOCKS % (1024 / RED_VALS) == 0, "reduce_final");
 
 // In-step checks of pfl_step: the check area after the reduction's final
 // values holds the first failing step (INT64_MAX if none), the step of the
@@ -327,11 +372,11 @@ struct Disp {
   template <int QN, int QP, int QS>
   static hipError_t reduce(const DevParams& P, int fields, const void* pops, const void* hist, int hp,
                            double* red, hipStream_t s) {
-    hipLaunchKernelGGL((reduce_kernel<QN, QP, QS, ST, HT>), dim3(RED_BLOCKS), dim3(BT), 0, s, P, fields,
+    hipLaunchKernelGGL((reduce_kernel<QN, QP, QS, ST, HT>), dim3(RED_BLOCKS), dim3(RBT), 0, s, P, fields,
                        (const typename Store<ST>::raw*)pops, (const HT*)hist, hp, red);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_final, dim3(1), dim3(64), 0, s, red);
+    hipLaunchKernelGGL(reduce_final, dim3(1), dim3(1024), 0, s, red);
     return hipGetLastError();
   }
 };
