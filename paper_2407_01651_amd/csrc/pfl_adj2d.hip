@@ -85,15 +85,26 @@ __global__ __launch_bounds__(256) void adj_init_kernel(const DevParams P, int fi
   S[3 * N + n] = (double)bid;
 }
 
+// Adds the sum v of parameter b: k (= -k1 gradient), Omega, then the radii.
+__device__ __forceinline__ void add_init_param(int b, double v, double* dparams) {
+  if (b == 0) dparams[1] -= v;
+  else dparams[b + 1] += v;
+}
+
+// Sums of parameter b = blockIdx.x over the nodes, in the blockIdx.y-th of
+// gridDim.y stretches: added to dparams when there is one, left in part
+// otherwise.  (One block per parameter reads the two planes of a 512^2 grid in
+// 576 us; 64 stretches and the sum over them take 9.)
 __global__ __launch_bounds__(256) void adj_init_sum_kernel(long long N, const double* __restrict__ S,
-                                                           int nbub, double* __restrict__ dparams) {
-  // block 0: k (= -k1 gradient), block 1: Omega, block 2 + b: radius of bubble b
-  const int b = blockIdx.x;
+                                                           double* __restrict__ part, double* __restrict__ dparams) {
+  const int b = blockIdx.x, g = blockIdx.y, G = gridDim.y;
+  const long long len = (N + G - 1) / G, n0 = len * g, n1 = n0 + len < N ? n0 + len : N;
   double a = 0.0;
-  for (long long n = threadIdx.x; n < N; n += 256) {
+#pragma unroll 4
+  for (long long n = n0 + threadIdx.x; n < n1; n += 256) {
     if (b == 0) a += S[n];
     else if (b == 1) a += S[N + n];
-    else if ((int)S[3 * N + n] == b - 2) a += S[2 * N + n];
+    else a += (int)S[3 * N + n] == b - 2 ? S[2 * N + n] : 0.0;
   }
   __shared__ double s[256];
   s[threadIdx.x] = a;
@@ -103,10 +114,24 @@ __global__ __launch_bounds__(256) void adj_init_sum_kernel(long long N, const do
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    if (b == 0) dparams[1] -= s[0];
-    else if (b == 1) dparams[2] += s[0];
-    else dparams[3 + (b - 2)] += s[0];
+    if (G == 1) add_init_param(b, s[0], dparams);
+    else part[(long long)b * G + g] = s[0];
   }
+}
+
+// The G <= 64 stretch sums of parameter blockIdx.x, by one wave in a fixed order.
+__global__ __launch_bounds__(64) void adj_init_total_kernel(int G, const double* __restrict__ part,
+                                                            double* __restrict__ dparams) {
+  const int b = blockIdx.x;
+  double a = (int)threadIdx.x < G ? part[(long long)b * G + threadIdx.x] : 0.0;
+  for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
+  if (threadIdx.x == 0) add_init_param(b, a, dparams);
+}
+
+// Stretches of the sums over N nodes: one per 4096 nodes, at most 64.
+int init_stretches(long long N) {
+  const long long g = (N + 4095) / 4096;
+  return g < 64 ? (int)g : 64;
 }
 
 }  // namespace
@@ -119,8 +144,10 @@ size_t adj_scratch_bytes(int nx, int ny, int store) {
   const size_t nb = (size_t)((N + 255) / 256);
   const size_t tiles = (size_t)((nx + TX - 1) / TX) * (size_t)((ny + TY - 1) / TY);
   const size_t bytes = part_offset(N, elem) + 3 * (nb > tiles ? nb : tiles) * sizeof(double);
-  // the initial-state adjoint uses four FP64 planes of the same buffer
-  const size_t init = 4 * (size_t)N * sizeof(double);
+  // the initial-state adjoint uses four FP64 planes of the same buffer and,
+  // with more than one stretch, its sums of each parameter
+  const int g = init_stretches(N);
+  const size_t init = (4 * (size_t)N + (g > 1 ? (size_t)(2 + MAX_BUBBLES) * g : 0)) * sizeof(double);
   return bytes > init ? bytes : init;
 }
 
@@ -175,7 +202,12 @@ hipError_t launch_adj_init2d(const DevParams& P, int fields, int store, const vo
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(adj_init_sum_kernel, dim3(2 + P.nbub), dim3(256), 0, s, P.N, S, P.nbub, dparams);
+  const int G = init_stretches(P.N), np = 2 + P.nbub;
+  double* part = S + 4 * P.N;
+  hipLaunchKernelGGL(adj_init_sum_kernel, dim3(np, G), dim3(256), 0, s, P.N, S, part, dparams);
+  e = hipGetLastError();
+  if (e != hipSuccess || G == 1) return e;
+  hipLaunchKernelGGL(adj_init_total_kernel, dim3(np), dim3(64), 0, s, G, part, dparams);
   return hipGetLastError();
 }
 
