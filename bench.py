@@ -38,7 +38,7 @@ PROFILES = {
         (CSRC + "pfl_step3d.hip", CSRC + "pfl_step3d_lowp.hip", CSRC + "pfl_step3d.h",
          CSRC + "pfl_step3d_f64.h", CSRC + "pfl_step3d_impl.h", CSRC + "pfl_util.h", CSRC + "pfl_dev.h", "paper_2407_01651_amd/build.py")),
     2: ("profiles/step2d_coupled2d_2048.md",
-        (CSRC + "pfl_step2d.hip", CSRC + "pfl_step2d_lowp.hip", CSRC + "pfl_step2d_impl.h",
+        (CSRC + "pfl_step2d.hip", CSRC + "pfl_step2d_lowp.hip", CSRC + "pfl_step2d_f64.h", CSRC + "pfl_step2d_impl.h",
          CSRC + "pfl_step2d.h", CSRC + "pfl_util.h", CSRC + "pfl_dev.h", "paper_2407_01651_amd/build.py")),
 }
 DEFAULT_VARIANTS = ("coupled3d_256:f32,coupled3d_256:f16,coupled3d_256:bf16,"

@@ -1,5 +1,5 @@
-// Fused 2D time step: one launch advances every active population set by
-// one step (pull streaming, moments, isotropic stencils, anisotropy,
+// Fused 2D time step in FP32 compute (FP32, FP16 and BF16 storage): one launch
+// advances every active population set by one step (pull streaming, moments, isotropic stencils, anisotropy,
 // forces, MRT collisions in closed form, time-stretched AAC store, history).
 //
 // Work decomposition: a workgroup owns a tile of nodes (StepTile: 32 x 8 with
@@ -10,10 +10,9 @@
 // Populations live in SoA planes (x fastest), post-collision at their source
 // node, so a node pulls f_i(x) from x - c_i; a population that would cross a
 // wall is read back from the node's own opposite slot (half-way bounce-back).
-// FP32 and 16-bit planes hold deviations f_i - w_i m_ref from the bulk-liquid
-// rest state and the collisions are written in those deviations, so that the
-// bulk, where f_i is close to w_i m_ref, rounds small numbers; FP64 planes
-// hold full populations.
+// The planes hold deviations f_i - w_i m_ref from the bulk-liquid rest state and
+// the collisions are written in those deviations, so that the bulk, where f_i is
+// close to w_i m_ref, rounds small numbers.
 //
 // Tiles whose pulls stay inside the domain take a fast path: every load and
 // store is a scalar base plus a 32-bit byte offset, one integer add per
@@ -84,13 +83,9 @@ void step2d_kernel(const DevParams P,
 
   // ---- phase A1: own node populations and moments
   CT fns[NS ? QN : 1], fph[PHI ? QP : 1], fps[PSI ? QS : 1], fc[CC ? QS : 1], fth[TH ? QS : 1];
-  // Moments are rest value + sum of stored values: phi = r_phi + dphi, ...
-  // Deviation storage (FP32, FP16, BF16) has r = (1, -1, C_ref, theta0);
-  // FP64 storage holds full populations, r = 0, and keeps the plain
-  // equilibrium forms below so its rounding follows the definitions.
-  constexpr bool DEV = !std::is_same<ST, double>::value;
-  const CT r_phi = DEV ? CT(1) : CT(0), r_psi = DEV ? CT(-1) : CT(0);
-  const CT r_C = DEV ? K.C_ref : CT(0), r_H = DEV ? K.theta0 : CT(0);
+  // Moments are rest value + sum of stored deviations: phi = r_phi + dphi, ...
+  const CT r_phi = CT(1), r_psi = CT(-1);
+  const CT r_C = K.C_ref, r_H = K.theta0;
   CT phi = CT(1), psi = CT(-1), C = CT(0), H = CT(0), U = K.U0, jx = CT(0), jy = CT(0);
   CT dphi = CT(0), dpsi = CT(0), dC = CT(0), dH = CT(0);
   // history and grain id of the own node, loaded early so that their latency
@@ -463,68 +458,36 @@ void step2d_kernel(const DevParams P,
       const CT cb = cx * bx + cy * by, cv = cx * vx + cy * vy;
       return rho * CT(LN::w[j]) * ((cb - cv) * CT(3) + (cb * cb - cv * cv) * CT(4.5) - (bx * bx + by * by - vv) * CT(1.5));
     };
-    if constexpr (sizeof(CT) == 4) {
-      // FP32 compute: the same collision in moment form.  On the 4th-order
-      // isotropic lattice the traceless stress moments of f^eq and of F/2 are
-      // rho T:vv and T:(vF + cs2 v grad(rho)) (symmetrised), and for i > 0
-      // f_i^eq + F_i/2 = w_i [A + c.v (3 rho + 4.5 (rho c.v + c.F) + 1.5 c.grad(rho)) + 1.5 c.F]
-      // with A = 3p - 1.5 rho v.v - 1.5 v.F; f_0^eq + F_0/2 = w_0 A - 3p.
-      const CT r = CT(1) - s_nu;
-      const CT A = CT(3) * p - CT(1.5) * rho * vv - CT(1.5) * vF;
-      CT s1 = CT(0), s2 = CT(0);
-#pragma unroll
-      for (int i = 1; i < QN; ++i) {
-        const int t1 = LN::c[i][0] * LN::c[i][0] - LN::c[i][1] * LN::c[i][1], t2 = LN::c[i][0] * LN::c[i][1];
-        if (t1 > 0) s1 += fns[i]; else if (t1 < 0) s1 -= fns[i];
-        if (t2 > 0) s2 += fns[i]; else if (t2 < 0) s2 -= fns[i];
-      }
-      const CT m1 = s1 - rho * (vx * vx - vy * vy) + (vx * Fx - vy * Fy) + CT(1.0 / 3) * (vx * grx - vy * gry);
-      const CT m2 = s2 - rho * vx * vy + CT(0.5) * (vx * Fy + vy * Fx) + CT(1.0 / 6) * (vx * gry + vy * grx);
-      const CT q1 = CT(0.25) * r * m1, q2 = CT(0.25) * r * m2;
-      const CT rho3 = CT(3) * rho;
-      auto post = [&](int i) -> CT {
-        const CT cx = CT(LN::c[i][0]), cy = CT(LN::c[i][1]);
-        const CT w = CT(LN::w[i]);
-        if (i == 0) return w * A - CT(3) * p;
-        const CT cv = cx * vx + cy * vy, cF = cx * Fx + cy * Fy, cg = cx * grx + cy * gry;
-        const CT t = cv * (rho3 + CT(4.5) * (rho * cv + cF) + CT(1.5) * cg) + CT(1.5) * cF + A;
-        return w * t + ((cx * cx - cy * cy) * q1 + (cx * cy) * q2);
-      };
-#pragma unroll
-      for (int i = 0; i < QN; ++i) {
-        CT fs = post(i);
-        if (const int kind = nee_out(i)) fs = post(LN::opp[i]) + nee(LN::opp[i], kind);
-        st(P.o_ns, i, fs);
-      }
-    } else {
-    CT fneq[QN], fhalf[QN];
-    CT m1 = CT(0), m2 = CT(0);   // projections on c_x^2 - c_y^2 and c_x c_y
-#pragma unroll
-    for (int i = 0; i < QN; ++i) {
-      const CT cx = CT(LN::c[i][0]), cy = CT(LN::c[i][1]);
-      const CT cv = cx * vx + cy * vy;
-      const CT cF = cx * Fx + cy * Fy;
-      const CT w = CT(LN::w[i]);
-      CT feq = w * p * CT(3) + rho * w * (cv * CT(3) + cv * cv * CT(4.5) - vv * CT(1.5));
-      if (i == 0) feq -= p * CT(3);
-      const CT cg = cx * grx + cy * gry;
-      const CT Ft = w * (cv * cg * CT(3) + cF * CT(3) + (cv * cF - vF * CT(1.0 / 3)) * CT(9));
-      fhalf[i] = feq + CT(0.5) * Ft;
-      fneq[i] = fns[i] - feq + CT(0.5) * Ft;
-      m1 += (cx * cx - cy * cy) * fneq[i];
-      m2 += (cx * cy) * fneq[i];
-    }
+    // The collision in moment form.  On the 4th-order isotropic lattice the
+    // traceless stress moments of f^eq and of F/2 are rho T:vv and T:(vF + cs2 v grad(rho)) (symmetrised), and for i > 0
+    // f_i^eq + F_i/2 = w_i [A + c.v (3 rho + 4.5 (rho c.v + c.F) + 1.5 c.grad(rho)) + 1.5 c.F]
+    // with A = 3p - 1.5 rho v.v - 1.5 v.F; f_0^eq + F_0/2 = w_0 A - 3p.
     const CT r = CT(1) - s_nu;
+    const CT A = CT(3) * p - CT(1.5) * rho * vv - CT(1.5) * vF;
+    CT s1 = CT(0), s2 = CT(0);
+#pragma unroll
+    for (int i = 1; i < QN; ++i) {
+      const int t1 = LN::c[i][0] * LN::c[i][0] - LN::c[i][1] * LN::c[i][1], t2 = LN::c[i][0] * LN::c[i][1];
+      if (t1 > 0) s1 += fns[i]; else if (t1 < 0) s1 -= fns[i];
+      if (t2 > 0) s2 += fns[i]; else if (t2 < 0) s2 -= fns[i];
+    }
+    const CT m1 = s1 - rho * (vx * vx - vy * vy) + (vx * Fx - vy * Fy) + CT(1.0 / 3) * (vx * grx - vy * gry);
+    const CT m2 = s2 - rho * vx * vy + CT(0.5) * (vx * Fy + vy * Fx) + CT(1.0 / 6) * (vx * gry + vy * grx);
+    const CT q1 = CT(0.25) * r * m1, q2 = CT(0.25) * r * m2;
+    const CT rho3 = CT(3) * rho;
     auto post = [&](int i) -> CT {
       const CT cx = CT(LN::c[i][0]), cy = CT(LN::c[i][1]);
-      return fhalf[i] + r * ((cx * cx - cy * cy) * m1 * CT(0.25) + (cx * cy) * m2 * CT(0.25));
+      const CT w = CT(LN::w[i]);
+      if (i == 0) return w * A - CT(3) * p;
+      const CT cv = cx * vx + cy * vy, cF = cx * Fx + cy * Fy, cg = cx * grx + cy * gry;
+      const CT t = cv * (rho3 + CT(4.5) * (rho * cv + cF) + CT(1.5) * cg) + CT(1.5) * cF + A;
+      return w * t + ((cx * cx - cy * cy) * q1 + (cx * cy) * q2);
     };
 #pragma unroll
     for (int i = 0; i < QN; ++i) {
       CT fs = post(i);
       if (const int kind = nee_out(i)) fs = post(LN::opp[i]) + nee(LN::opp[i], kind);
       st(P.o_ns, i, fs);
-    }
     }
   }
 
@@ -543,8 +506,7 @@ void step2d_kernel(const DevParams P,
       const CT cx = CT(LP::c[i][0]), cy = CT(LP::c[i][1]);
       const CT w = CT(LP::w[i]);
       // equilibrium w phi (1 + c.v/cs2), less w under deviation storage
-      if constexpr (DEV) feq[i] = w * dphi + w * phi * (cx * vx + cy * vy) * CT(1.0 / LP::cs2);
-      else feq[i] = w * phi * (CT(1) + (cx * vx + cy * vy) * CT(1.0 / LP::cs2));
+      feq[i] = w * dphi + w * phi * (cx * vx + cy * vy) * CT(1.0 / LP::cs2);
       G[i] = w * (cx * gx_ + cy * gy_) * CT(1.0 / LP::cs2);
       jx_ += cx * (fph[i] - feq[i]); jy_ += cy * (fph[i] - feq[i]);
       gjx += cx * G[i]; gjy += cy * G[i];
@@ -648,10 +610,7 @@ void step2d_kernel(const DevParams P,
       // model's H, so the rest equilibrium rho H + (w - 1) theta is
       // H + (w - 1) theta, less w theta0: dH + (w - 1) dtheta
       CT geq = w * dtheta + w * (cx * Hvx + cy * Hvy) * CT(3);
-      if (i == 0) {
-        if constexpr (DEV) geq = K.varheat ? dH + (w - CT(1)) * dtheta : -h + w * dtheta;
-        else geq = H + (w - CT(1)) * theta;
-      }
+      if (i == 0) geq = K.varheat ? dH + (w - CT(1)) * dtheta : -h + w * dtheta;
       const CT G = w * (cx * dx_ + cy * dy_) * CT(3);
       CT gs = geq + (CT(1) - s1) * (cx * jx_ + cy * jy_) * CT(0.5) + (CT(1) - CT(0.5) * s1) * G;
       if (far_out(i)) gs = CT(2) * w * (K.theta0 - r_H) - gs;   // anti-bounce-back to theta0
