@@ -302,9 +302,10 @@ int pfl_create(pfl_ctx** out, const pfl_params* p, const pfl_buffers* bufs, void
     const bool wide16 = p->dim == 2 && (p->fields & PFL_NS) && (p->fields & PFL_PHI);
     const bool full_lines = p->store == PFL_F64 || p->store == PFL_F32 ||
                             ((p->store == PFL_F16 || p->store == PFL_BF16) && wide16);
+    const bool beyond_llc = 2 * (L.pops_bytes + L.hist_bytes) > ((size_t)256 << 20);
     d.nt = p->write_policy == PFL_WRITE_STREAM ||
-           (p->write_policy == PFL_WRITE_AUTO && full_lines &&
-            2 * (L.pops_bytes + L.hist_bytes) > ((size_t)256 << 20));
+           (p->write_policy == PFL_WRITE_AUTO && full_lines && beyond_llc);
+    d.touch = beyond_llc;
     d.step_ctr = 0;
   }
   uint8_t* aux = (uint8_t*)bufs->aux;

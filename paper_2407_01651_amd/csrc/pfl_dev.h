@@ -165,6 +165,7 @@ struct DevParams {
   int plane32;                 // byte offsets within one plane fit in 32 bits
   int zc;                      // 3D: z planes per workgroup chunk (0: chosen at the launch)
   int cus;                     // compute units of the device
+  int touch;                   // 3D, 16-bit storage: rows of the next plane touched ahead
   int le1;                     // AAC form for Le = O(1): a_n = a_s^2 F(U), no F in D_psi and S_psi
   int vel;                     // velocity sides, bits as sym (also set in far: psi, C, theta see a far-field side)
   double vin[3];               // velocity of the velocity sides

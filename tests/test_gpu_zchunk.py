@@ -34,3 +34,24 @@ def test_chosen_chunks_give_the_state_of_one_chunk(nx, ny, nz, over, store, monk
         states.append((sim.get_state().cpu(), sim.macros()["vx"].cpu()))
         sim.close()
     assert all(torch.equal(a, b) for a, b in zip(*states))
+
+
+@pytest.mark.parametrize("store", ["f16", "bf16"])
+def test_chunks_agree_on_a_state_beyond_the_last_level_cache(store, monkeypatch):
+    """The step touches the next plane's rows ahead on such a state (2 x 159 MB): ragged
+    tiles, chunks with a remainder and the last planes of a chunk and of the grid."""
+    import paper_2407_01651_amd as pfl
+    w = workloads.small(dim=3, nx=131, ny=133, nz=67, seed=8)
+    states = []
+    for chunk in (None, "67", "9"):
+        if chunk is None:
+            monkeypatch.delenv("PFL_ZCHUNK", raising=False)
+        else:
+            monkeypatch.setenv("PFL_ZCHUNK", chunk)
+        sim = pfl.Sim(w, store=store)
+        assert 2 * (sim.sizes.pops_bytes + sim.sizes.hist_bytes) > 256 << 20
+        sim.init_fields()
+        sim.step(3)
+        states.append(sim.get_state())
+        sim.close()
+    assert torch.equal(states[0], states[1]) and torch.equal(states[0], states[2])
