@@ -67,6 +67,8 @@ class CheckpointedRun:
         self.rstream = torch.cuda.Stream(device=self.sim.device) if self.overlap else None
         self.rsim = Sim(w, store=store, device=device, stream=self.rstream) if self.overlap else self.sim
         if self.overlap:
+            # its buffers may be memory that work still queued on the main stream uses
+            self.rstream.wait_stream(self.sim.stream)
             self.rsim.init_fields()        # grain map and angles for its pfl_step_raw
         self.taped = bool(taped)
         self.ckpts = []
