@@ -7,6 +7,7 @@
 
 namespace pfl {
 
+
 constexpr int TX = 32, TY = 8, NT = TX * TY;
 // The step kernel's tile, one node per thread: with the flow and the bubble
 // phase both active (two halo rings), 32 x 8 nodes, or 64 x 4 with 16-bit
@@ -44,6 +45,9 @@ struct StepTile {
 // mirror node's population with the normal component reversed) on each axis.
 // SYM: the grid has symmetry planes or far-field sides (a separate
 // instantiation, so that grids without them carry none of that code).
+// Addresses are chosen by selects of 32-bit offsets and of plane starts, not
+// by branches, so that the loads of a set leave together: edge tiles are what a
+// launch on a small grid waits for.
 template <int Q, class ST, class CT, bool SYM = false>
 __device__ __forceinline__ void pull_general(const typename Store<ST>::raw* __restrict__ base,
                                              const DevParams& P, int x, int y, CT f[Q]) {
@@ -58,8 +62,10 @@ __device__ __forceinline__ void pull_general(const typename Store<ST>::raw* __re
   for (int i = 0; i < Q; ++i) {
     const int cx = L::c[i][0] + 1, cy = L::c[i][1] + 1;
     const bool b = ax.wall[cx] || ay.wall[cy];
-    const int j = SYM ? pulled_population<Q>(i, m) : i;
-    const long long e = b ? (long long)L::opp[i] * N + own : (long long)j * N + own + ax.off[cx] + ay.off[cy];
+    const int off = b ? 0 : ax.off[cx] + ay.off[cy];
+    const long long plane = SYM ? (long long)(b ? L::opp[i] : pulled_population<Q>(i, m)) * N
+                                : (b ? L::opp[i] * N : i * N);
+    const long long e = plane + own + off;
     f[i] = Store<ST>::template ld<CT>(base + e);
   }
 }
@@ -85,6 +91,10 @@ __device__ __forceinline__ void pull(bool fast, const typename Store<ST>::raw* _
     pull_fast<Q, ST, CT>(base, P, nbyte, f);
   } else {
     pull_general<Q, ST, CT, SYM>(base, P, x, y, f);
+    // FP32 compute, built with reassociation: an end to the loads that the
+    // optimiser may not move, so that it neither joins them with the interior
+    // form's nor sums them as vectors; the sums keep the order of the source
+    if constexpr (sizeof(CT) == 4) asm volatile("");
   }
 }
 
