@@ -39,7 +39,9 @@ __device__ __forceinline__ int ring_slot(int p, int n) {
 // periodic wrap, half-way bounce-back at a wall or specular reflection at a
 // symmetry plane on each axis, from per-axis source offsets computed once
 // per node.
-template <int Q, class ST, class CT, bool SYM>
+// SEL: addresses by selects instead of branches, so that the loads of a set
+// leave together.
+template <int Q, class ST, class CT, bool SYM, bool SEL>
 __device__ __forceinline__ void pull3_general(const typename Store<ST>::raw* __restrict__ base,
                                               const DevParams& P, int x, int y, int z, CT f[Q]) {
   using L = Lat<Q>;
@@ -54,9 +56,16 @@ __device__ __forceinline__ void pull3_general(const typename Store<ST>::raw* __r
   for (int i = 0; i < Q; ++i) {
     const int cx = L::c[i][0] + 1, cy = L::c[i][1] + 1, cz = L::c[i][2] + 1;
     const bool b = ax.wall[cx] || ay.wall[cy] || az.wall[cz];
-    const int j = SYM ? pulled_population<Q>(i, m) : i;
-    const long long e = b ? (long long)L::opp[i] * N + own
-                          : (long long)j * N + (own + ax.off[cx] + ay.off[cy] + az.off[cz]);
+    long long e;
+    if constexpr (SEL) {
+      const int off = b ? 0 : ax.off[cx] + ay.off[cy] + az.off[cz];
+      const long long plane = SYM ? (long long)(b ? L::opp[i] : pulled_population<Q>(i, m)) * N
+                                  : (b ? L::opp[i] * N : i * N);
+      e = plane + own + off;
+    } else {
+      const int j = SYM ? pulled_population<Q>(i, m) : i;
+      e = b ? (long long)L::opp[i] * N + own : (long long)j * N + (own + ax.off[cx] + ay.off[cy] + az.off[cz]);
+    }
     f[i] = Store<ST>::template ld<CT>(base + e);
   }
 }
@@ -78,14 +87,14 @@ __device__ __forceinline__ void pull3_fast(const typename Store<ST>::raw* __rest
   }
 }
 
-template <int Q, class ST, class CT, bool SYM>
+template <int Q, class ST, class CT, bool SYM = false, bool SEL = false>
 __device__ __forceinline__ void pull3(bool fast, const typename Store<ST>::raw* __restrict__ base,
                                       const DevParams& P, int x, int y, int z, CT f[Q]) {
   if (fast) {
     const uint32_t nbyte = (uint32_t)((z * P.ny + y) * P.nx + x) * (uint32_t)sizeof(typename Store<ST>::raw);
     pull3_fast<Q, ST, CT>(base, P, nbyte, f);
   } else {
-    pull3_general<Q, ST, CT, SYM>(base, P, x, y, z, f);
+    pull3_general<Q, ST, CT, SYM, SEL>(base, P, x, y, z, f);
   }
 }
 

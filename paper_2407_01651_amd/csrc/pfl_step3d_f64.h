@@ -497,6 +497,11 @@ __global__ __launch_bounds__(Col3<double>::NT, FIELDS == 31 ? 1 : 2) void step3d
   constexpr int R = FLOWX ? 2 : 1;
   constexpr int AHEAD = FLOWX ? 2 : 1;     // phi runs this many planes ahead
   constexpr int NT = Col3<double>::NT, TX = Col3<double>::TX;
+  // general pulls by selects (256^3 coupled 4.67 -> 4.54 ms a step, 96^3 corner
+  // 117 -> 111 us), but not for a flow without the bubble phase, which is faster
+  // with branches (160 x 150^2 with psi and heat 463 us a step; selects 466).  The
+  // FP32-compute forms, built with reassociation, would round differently.
+  constexpr bool SEL = !NS || PHI;
   using ST = double;
   using PR = Pl<double, R>;
   using P1 = Pl<double, 1>;
@@ -508,6 +513,7 @@ __global__ __launch_bounds__(Col3<double>::NT, FIELDS == 31 ? 1 : 2) void step3d
   // beyond a high side), which a barrier separates from the next phase A.
   constexpr int NPH = 4, NPS = 4;
   const KP<double>& K = P.kd;
+  const ArgLines<double> args;
 
   __shared__ double s_phi[NPH * PR::N];
   __shared__ double s_psi[NPS * P1::N];
@@ -530,6 +536,7 @@ __global__ __launch_bounds__(Col3<double>::NT, FIELDS == 31 ? 1 : 2) void step3d
   const double* fin_c = fin + (size_t)(CC ? P.o_c : 0) * (size_t)N;
   const double* fin_th = fin + (size_t)(TH ? P.o_th : 0) * (size_t)N;
 
+  args.settle();
   ScMom ph0{}, ph1{}, ph2{};                // phi at planes t, t + 1, t + 2
   NsMom nsA{}, nsB{};                       // planes t (this step's phase C), t + 1
   ScMom psA{}, psB{}, cA{}, cB{}, thA{}, thB{};
@@ -542,7 +549,7 @@ __global__ __launch_bounds__(Col3<double>::NT, FIELDS == 31 ? 1 : 2) void step3d
       const bool fast = col.fast(P, p);
       int g[3];
       col.source(P, fast, lx, ly, p, g);
-      pull3<7, ST, double, SYM>(fast, fin_phi, P, g[0], g[1], g[2], rph);
+      pull3<7, ST, double, SYM, SEL>(fast, fin_phi, P, g[0], g[1], g[2], rph);
     }
   };
   auto pull_rest = [&](int p) {
@@ -551,10 +558,10 @@ __global__ __launch_bounds__(Col3<double>::NT, FIELDS == 31 ? 1 : 2) void step3d
     col.source(P, fast, lx, ly, p, g);
     auto all = [&](auto f) {
       constexpr bool F = decltype(f)::value;
-      if constexpr (PSI) pull3<7, ST, double, SYM>(F, fin_psi, P, g[0], g[1], g[2], rps);
-      if constexpr (CC) pull3<7, ST, double, SYM>(F, fin_c, P, g[0], g[1], g[2], rc);
-      if constexpr (NS) pull3<19, ST, double, SYM>(F, fin_ns, P, g[0], g[1], g[2], rns);
-      if constexpr (TH) pull3<7, ST, double, SYM>(F, fin_th, P, g[0], g[1], g[2], rth);
+      if constexpr (PSI) pull3<7, ST, double, SYM, SEL>(F, fin_psi, P, g[0], g[1], g[2], rps);
+      if constexpr (CC) pull3<7, ST, double, SYM, SEL>(F, fin_c, P, g[0], g[1], g[2], rc);
+      if constexpr (NS) pull3<19, ST, double, SYM, SEL>(F, fin_ns, P, g[0], g[1], g[2], rns);
+      if constexpr (TH) pull3<7, ST, double, SYM, SEL>(F, fin_th, P, g[0], g[1], g[2], rth);
     };
     if (fast) all(std::true_type{});
     else all(std::false_type{});
@@ -575,7 +582,7 @@ __global__ __launch_bounds__(Col3<double>::NT, FIELDS == 31 ? 1 : 2) void step3d
         int g[3];
         col.source(P, fast, k % PR::X - R, k / PR::X - R, p, g);
         double f[7];
-        pull3<7, ST, double, SYM>(fast, fin_phi, P, g[0], g[1], g[2], f);
+        pull3<7, ST, double, SYM, SEL>(fast, fin_phi, P, g[0], g[1], g[2], f);
         phi = sc_sum(f);
       }
       dst[k] = phi;
@@ -611,9 +618,9 @@ __global__ __launch_bounds__(Col3<double>::NT, FIELDS == 31 ? 1 : 2) void step3d
       double fp[7], fc[7], fn[19], j[3] = {0.0, 0.0, 0.0};
       auto all = [&](auto f) {
         constexpr bool F = decltype(f)::value;
-        if constexpr (PSI) pull3<7, ST, double, SYM>(F, fin_psi, P, g[0], g[1], g[2], fp);
-        if constexpr (CC) pull3<7, ST, double, SYM>(F, fin_c, P, g[0], g[1], g[2], fc);
-        if constexpr (NS) pull3<19, ST, double, SYM>(F, fin_ns, P, g[0], g[1], g[2], fn);
+        if constexpr (PSI) pull3<7, ST, double, SYM, SEL>(F, fin_psi, P, g[0], g[1], g[2], fp);
+        if constexpr (CC) pull3<7, ST, double, SYM, SEL>(F, fin_c, P, g[0], g[1], g[2], fc);
+        if constexpr (NS) pull3<19, ST, double, SYM, SEL>(F, fin_ns, P, g[0], g[1], g[2], fn);
       };
       if (fast) all(std::true_type{});
       else all(std::false_type{});
