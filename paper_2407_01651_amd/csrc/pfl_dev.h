@@ -212,6 +212,21 @@ struct ArgLines {
   __device__ __forceinline__ void settle() const { asm volatile("" ::"s"(sum)); }
 };
 
+// Addresses of one node in the Q planes of a set, each one add from the last.  A
+// product of plane and stride for each store takes some eight scalar
+// instructions, and a SIMD issues those of one wave at a time: FP64 128^2 coupled
+// 8.9 -> 8.7 us a step; FP32 8.5 -> 8.1, 1001 x 730 41.5 -> 40.5; 2048^2 FP16
+// 203 -> 199; 1024^2 alloy BF16 19.9 -> 18.9.
+template <int Q, class T>
+struct Planes {
+  T* at[Q];
+  __device__ __forceinline__ Planes(T* first, long long stride) {
+    at[0] = first;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) at[i] = at[i - 1] + stride;
+  }
+};
+
 // Whether the low (lo) or high boundary of axis a is a symmetry plane.
 __device__ __forceinline__ bool sym_side(const DevParams& P, int a, bool lo) {
   return (P.sym >> (lo ? a : 3 + a)) & 1;

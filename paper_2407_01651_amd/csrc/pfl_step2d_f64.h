@@ -87,20 +87,6 @@ __device__ __forceinline__ void put_set(double rest, double even, const double (
   }
 }
 
-// Addresses of one node in the Q planes of a set, each one add from the last (a
-// product of plane and stride for each store takes some eight scalar
-// instructions, and a wave that has its SIMD to itself waits for them: 128^2
-// coupled 8.9 -> 8.7 us a step, 200 x 400 column 16.9 -> 16.6).
-template <int Q>
-struct Planes {
-  double* at[Q];
-  __device__ __forceinline__ Planes(double* first, long long stride) {
-    at[0] = first;
-#pragma unroll
-    for (int i = 1; i < Q; ++i) at[i] = at[i - 1] + stride;
-  }
-};
-
 // One thread per node of the tile (StepTile).  Large grids are bound by HBM at
 // the waves the registers allow, small ones by the chain of latencies from the
 // pulls to the stores, so a thread issues its own pulls and its halo
@@ -411,7 +397,7 @@ void step2d_f64_kernel(const DevParams P, const double* __restrict__ fin, double
   // f_i^eq + F_i/2 = w_i [A + c.v (3 rho + 4.5 (rho c.v + c.F) + 1.5 c.grad(rho)) + 1.5 c.F]
   // with A = 3p - 1.5 rho v.v - 1.5 v.F; f_0^eq + F_0/2 = w_0 A - 3p.
   if constexpr (NS) {
-    const Planes<9> out(fout + (long long)P.o_ns * N + idx, N);
+    const Planes<9, double> out(fout + (long long)P.o_ns * N + idx, N);
     const double nu = (K.mu_g + (K.mu_l - K.mu_g) * phi) * rcp(rho);
     const double r = 1.0 - rcp(nu * 3.0 + 0.5);
     const double vx = v[0], vy = v[1], Fx = F[0], Fy = F[1], grx = gr[0], gry = gr[1];
@@ -465,7 +451,7 @@ void step2d_f64_kernel(const DevParams P, const double* __restrict__ fin, double
       pvs[a] = pv;
     }
     hst2(P.h_phiv, pvs[0], pvs[1]);
-    const Planes<QP> out(fout + (long long)P.o_phi * N + idx, N);
+    const Planes<QP, double> out(fout + (long long)P.o_phi * N + idx, N);
     put_set<QP>(LP::w[0] * phi, phi, E, D, [&](int i, double f) { st(out.at[i], f); });
   }
 
@@ -527,7 +513,7 @@ void step2d_f64_kernel(const DevParams P, const double* __restrict__ fin, double
       const double even = psi + S_psi + 0.5 * (S_psi - (first ? S_psi : h_S));
       const double g = -(1.0 - 0.5 * rate) * inv_as2 * LS::cs2;
       const double E[2] = {g * Nv[0], g * Nv[1]}, D[2] = {(1.0 - rate) * mps.J[0], (1.0 - rate) * mps.J[1]};
-      const Planes<5> out(fout + (long long)P.o_psi * N + idx, N);
+      const Planes<5, double> out(fout + (long long)P.o_psi * N + idx, N);
       put_set<5>(LS::w[0] * even, even, E, D, [&](int i, double f) {
         st(out.at[i], (stored5(i, f, -1.0) - (1.0 - an) * old[i]) * inv_an);
       });
@@ -555,7 +541,7 @@ void step2d_f64_kernel(const DevParams P, const double* __restrict__ fin, double
       Bs[a] = B;
     }
     hst2(P.h_B, Bs[0], Bs[1]);
-    const Planes<5> out(fout + (long long)P.o_c * N + idx, N);
+    const Planes<5, double> out(fout + (long long)P.o_c * N + idx, N);
     put_set<5>(LS::w[0] * C, C, E, D, [&](int i, double f) { st(out.at[i], stored5(i, f, 1.0)); });
   }
 
@@ -571,7 +557,7 @@ void step2d_f64_kernel(const DevParams P, const double* __restrict__ fin, double
       Hvs[a] = Hv;
     }
     hst2(P.h_Hv, Hvs[0], Hvs[1]);
-    const Planes<5> out(fout + (long long)P.o_th * N + idx, N);
+    const Planes<5, double> out(fout + (long long)P.o_th * N + idx, N);
     put_set<5>(H + (LS::w[0] - 1.0) * theta, theta, E, D, [&](int i, double f) { st(out.at[i], stored5(i, f, K.theta0)); });
   }
 }

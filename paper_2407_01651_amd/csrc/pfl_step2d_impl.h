@@ -436,18 +436,20 @@ void step2d_kernel(const DevParams P,
   constexpr bool LOWP = sizeof(typename Store<ST>::raw) == 2;
   constexpr int QMAX = NS ? QN : ((PHI && QP > QS) ? QP : QS);
   const RoundBits<LOWP ? (QMAX + 1) / 2 : 1> rb(LOWP ? round_seed(P, (uint32_t)idx) : 0u, LOWP && P.sr);
-  // store of population i of the set whose first plane is o
-  // (one address form for every grid: the plane's base is uniform, the node
-  // offset one 64-bit shift-add; a run-time choice between two forms would
-  // merge them into a VGPR pointer computed per store)
-  auto st = [&](int o, int i, CT v) {
-    typename Store<ST>::raw* p = fout + (long long)(o + i) * N + idx;
+  // store of population i of a set (one address form for every grid: a run-time
+  // choice between a 32-bit and a 64-bit one would compute both)
+  auto st = [&](const auto& out, int i, CT v) {
     uint32_t r = 0u;
     if constexpr (LOWP) r = rb.bits(i);
-    store_pop<ST, CT, STREAM>(P, p, v, r);
+    store_pop<ST, CT, STREAM>(P, out.at[i], v, r);
   };
   auto hst = [&](int plane, CT v) {
     put<STREAM, HT>(hist + (long long)plane * N + idx, (HT)v);
+  };
+  auto hst2 = [&](int plane, CT v0, CT v1) {
+    HT* at = hist + (long long)plane * N + idx;
+    put<STREAM, HT>(at, (HT)v0);
+    put<STREAM, HT>(at + N, (HT)v1);
   };
 
   // ---- NS collision: f* = feq + F/2 + (1 - s_nu) P_s (f - feq + F/2),
@@ -506,11 +508,12 @@ void step2d_kernel(const DevParams P,
       const CT t = cv * (rho3 + CT(4.5) * (rho * cv + cF) + CT(1.5) * cg) + CT(1.5) * cF + A;
       return w * t + ((cx * cx - cy * cy) * q1 + (cx * cy) * q2);
     };
+    const Planes<QN, raw> out(fout + (long long)P.o_ns * N + idx, N);
 #pragma unroll
     for (int i = 0; i < QN; ++i) {
       CT fs = post(i);
       if (const int kind = nee_out(i)) fs = post(LN::opp[i]) + nee(LN::opp[i], kind);
-      st(P.o_ns, i, fs);
+      st(out, i, fs);
     }
   }
 
@@ -535,16 +538,16 @@ void step2d_kernel(const DevParams P,
       gjx += cx * G[i]; gjy += cy * G[i];
     }
     const CT inv_fn = CT(1.0 / LP::flux_norm);
+    const Planes<QP, raw> out(fout + (long long)P.o_phi * N + idx, N);
 #pragma unroll
     for (int i = 0; i < QP; ++i) {
       const CT cx = CT(LP::c[i][0]), cy = CT(LP::c[i][1]);
       const CT Pf = (cx * jx_ + cy * jy_) * inv_fn;        // projector on the flux moments
       const CT PG = (cx * gjx + cy * gjy) * inv_fn;
       const CT fs = feq[i] + (CT(1) - s1) * Pf + CT(0.5) * G[i] + CT(0.5) * (CT(1) - s1) * PG;
-      st(P.o_phi, i, fs);
+      st(out, i, fs);
     }
-    hst(P.h_phiv, phivx);
-    hst(P.h_phiv + 1, phivy);
+    hst2(P.h_phiv, phivx, phivy);
   }
 
   // ---- AAC collision with the time-stretched store
@@ -560,6 +563,7 @@ void step2d_kernel(const DevParams P,
     }
     const CT inv_as2 = P.le1 ? rcp(as2) : inv_an;
     const CT gNx = -Nx * inv_as2, gNy = -Ny * inv_as2;  // G_i = -w_i c_i.N / a_s^2
+    const Planes<QS, raw> out(fout + (long long)P.o_psi * N + idx, N);
 #pragma unroll
     for (int i = 0; i < QS; ++i) {
       const CT cx = CT(LS::c[i][0]), cy = CT(LS::c[i][1]);
@@ -575,7 +579,7 @@ void step2d_kernel(const DevParams P,
                                     (P.wall[1] && (y + dy < 0 || y + dy >= P.ny)));
       const CT old = across ? fps[LS::opp[i]] : s_fps[i][ry + dy][rx + dx];
       const CT fs = (fstar - (CT(1) - an) * old) * inv_an;
-      st(P.o_psi, i, fs);
+      st(out, i, fs);
     }
   }
 
@@ -600,6 +604,7 @@ void step2d_kernel(const DevParams P,
     for (int i = 0; i < QS; ++i) { jx_ += CT(LS::c[i][0]) * fc[i]; jy_ += CT(LS::c[i][1]) * fc[i]; }
     jx_ -= Bx; jy_ -= By;
     const CT dBx = Bx - Bpx, dBy = By - Bpy;
+    const Planes<QS, raw> out(fout + (long long)P.o_c * N + idx, N);
 #pragma unroll
     for (int i = 0; i < QS; ++i) {
       const CT cx = CT(LS::c[i][0]), cy = CT(LS::c[i][1]);
@@ -608,10 +613,9 @@ void step2d_kernel(const DevParams P,
       const CT G = w * (cx * dBx + cy * dBy) * CT(3);
       CT fs = feq + (CT(1) - s1) * (cx * jx_ + cy * jy_) * CT(0.5) + (CT(1) - CT(0.5) * s1) * G;
       if (far_out(i)) fs = CT(2) * w * (CT(1) - r_C) - fs;      // anti-bounce-back to C = 1
-      st(P.o_c, i, fs);
+      st(out, i, fs);
     }
-    hst(P.h_B, Bx);
-    hst(P.h_B + 1, By);
+    hst2(P.h_B, Bx, By);
   }
 
   // ---- heat collision
@@ -625,6 +629,7 @@ void step2d_kernel(const DevParams P,
     for (int i = 0; i < QS; ++i) { jx_ += CT(LS::c[i][0]) * fth[i]; jy_ += CT(LS::c[i][1]) * fth[i]; }
     jx_ -= Hvx; jy_ -= Hvy;
     const CT dx_ = Hvx - Hpx, dy_ = Hvy - Hpy;
+    const Planes<QS, raw> out(fout + (long long)P.o_th * N + idx, N);
 #pragma unroll
     for (int i = 0; i < QS; ++i) {
       const CT cx = CT(LS::c[i][0]), cy = CT(LS::c[i][1]);
@@ -637,10 +642,9 @@ void step2d_kernel(const DevParams P,
       const CT G = w * (cx * dx_ + cy * dy_) * CT(3);
       CT gs = geq + (CT(1) - s1) * (cx * jx_ + cy * jy_) * CT(0.5) + (CT(1) - CT(0.5) * s1) * G;
       if (far_out(i)) gs = CT(2) * w * (K.theta0 - r_H) - gs;   // anti-bounce-back to theta0
-      st(P.o_th, i, gs);
+      st(out, i, gs);
     }
-    hst(P.h_Hv, Hvx);
-    hst(P.h_Hv + 1, Hvy);
+    hst2(P.h_Hv, Hvx, Hvy);
   }
 
   if constexpr (PSI) {
