@@ -719,16 +719,31 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
           constexpr bool LOWP = sizeof(raw) == 2;
           constexpr int QMAX = NS ? QN : QS;
           const RoundBits<LOWP ? (QMAX + 1) / 2 : 1> rb(LOWP ? round_seed(P, (uint32_t)idx) : 0u, LOWP && P.sr);
-          // store of population i of the set whose first plane is o
-          auto st = [&](int o, int i, CT val) {
-            const int plane = o + i;
-            raw* ptr = P.plane32 ? at_byte<ST>(fout + (size_t)plane * (size_t)N, nbyte) : fout + (long long)plane * N + idx;
+          // store of population i of the set whose first plane is o: 16-bit storage
+          // without kept populations takes addresses an add apart (256^3 BF16 coupled
+          // 2.18 -> 2.10 ms a step, 90 x 70 x 50 77 -> 74 us, 160^3 FP16 alloy 178 ->
+          // 172).  The kernels with kept ones spill with the register pair that it
+          // takes (256^3 FP16 1.95 -> 2.38 ms), and the FP32 corner gets slower (150^3
+          // 373 -> 379 us).
+          constexpr bool RUN = sizeof(raw) == 2 && !KEEP16;
+          auto planes = [&](int o, auto q) {
+            if constexpr (RUN) return Planes<decltype(q)::value, raw>(fout + (long long)o * N + idx, N);
+            else return o;
+          };
+          auto st = [&](const auto& o, int i, CT val) {
+            raw* ptr;
+            if constexpr (RUN) {
+              ptr = o.at[i];
+            } else {
+              const int plane = o + i;
+              ptr = P.plane32 ? at_byte<ST>(fout + (size_t)plane * (size_t)N, nbyte) : fout + (long long)plane * N + idx;
+            }
             uint32_t r = 0u;
             if constexpr (LOWP) r = rb.bits(i);
             store_pop<ST, CT, STREAM>(P, ptr, val, r);
           };
           auto hst = [&](int plane, CT val) {
-            HT* q = P.plane32 ? (HT*)((char*)(hist + (size_t)plane * (size_t)N) + hbyte) : hist + (long long)plane * N + idx;
+            HT* q = !RUN && P.plane32 ? (HT*)((char*)(hist + (size_t)plane * (size_t)N) + hbyte) : hist + (long long)plane * N + idx;
             put<STREAM, HT>(q, (HT)val);
           };
 
@@ -807,11 +822,12 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
                 return rho * CT(LN::w[j]) *
                        ((cb - cv) * CT(3) + (cb * cb - cv * cv) * CT(4.5) - (bx * bx + by * by + bz * bz - vv) * CT(1.5));
               };
+              const auto out = planes(P.o_ns, std::integral_constant<int, QN>{});
 #pragma unroll
               for (int i = 0; i < QN; ++i) {
                 CT fs = post(i);
                 if (const int kind = nee_out(i)) fs = post(LN::opp[i]) + nee(LN::opp[i], kind);
-                st(P.o_ns, i, fs);
+                st(out, i, fs);
               }
             }
           }
@@ -840,12 +856,13 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
               gj[0] += cx * G[i]; gj[1] += cy * G[i]; gj[2] += cz * G[i];
             }
             const CT inv_fn = CT(1.0 / LP::flux_norm);
+            const auto out = planes(P.o_phi, std::integral_constant<int, QP>{});
 #pragma unroll
             for (int i = 0; i < QP; ++i) {
               const CT cx = CT(LP::c[i][0]), cy = CT(LP::c[i][1]), cz = CT(LP::c[i][2]);
               const CT Pf = (cx * jf[0] + cy * jf[1] + cz * jf[2]) * inv_fn;
               const CT PG = (cx * gj[0] + cy * gj[1] + cz * gj[2]) * inv_fn;
-              st(P.o_phi, i, feq[i] + (CT(1) - s1) * Pf + CT(0.5) * G[i] + CT(0.5) * (CT(1) - s1) * PG);
+              st(out, i, feq[i] + (CT(1) - s1) * Pf + CT(0.5) * G[i] + CT(0.5) * (CT(1) - s1) * PG);
             }
 #pragma unroll
             for (int a = 0; a < 3; ++a) hst(P.h_phiv + a, phiv[a]);
@@ -870,6 +887,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
             const raw* own_psi = fin_psi + idx;
             const int n3[3] = {P.nx, P.ny, P.nz};
             const int xyz[3] = {x, y, z};
+            const auto out = planes(P.o_psi, std::integral_constant<int, QS>{});
 #pragma unroll
             for (int i = 0; i < QS; ++i) {
               const CT cx = CT(LS::c[i][0]), cy = CT(LS::c[i][1]), cz = CT(LS::c[i][2]);
@@ -887,7 +905,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
               }
               const CT old = across ? fps[LS::opp[i]]
                                     : Store<ST>::template ld<CT>(own_psi + (long long)i * N);
-              st(P.o_psi, i, (fstar - (CT(1) - an) * old) * inv_an);
+              st(out, i, (fstar - (CT(1) - an) * old) * inv_an);
             }
           }
 
@@ -913,6 +931,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
               if (LS::c[i][1]) jf[1] += CT(LS::c[i][1]) * fc[i];
               if (LS::c[i][2]) jf[2] += CT(LS::c[i][2]) * fc[i];
             }
+            const auto out = planes(P.o_c, std::integral_constant<int, QS>{});
 #pragma unroll
             for (int i = 0; i < QS; ++i) {
               const CT cx = CT(LS::c[i][0]), cy = CT(LS::c[i][1]), cz = CT(LS::c[i][2]);
@@ -921,7 +940,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
               const CT G = w * (cx * dB[0] + cy * dB[1] + cz * dB[2]) * CT(1.0 / LS::cs2);
               CT fs = feq + (CT(1) - s1) * (cx * jf[0] + cy * jf[1] + cz * jf[2]) * CT(0.5) + (CT(1) - CT(0.5) * s1) * G;
               if (far_out(i)) fs = CT(2) * w * (CT(1) - r_C) - fs;      // anti-bounce-back to C = 1
-              st(P.o_c, i, fs);
+              st(out, i, fs);
             }
 #pragma unroll
             for (int a = 0; a < 3; ++a) hst(P.h_B + a, B[a]);
@@ -941,6 +960,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
               if (LS::c[i][1]) jf[1] += CT(LS::c[i][1]) * fth[i];
               if (LS::c[i][2]) jf[2] += CT(LS::c[i][2]) * fth[i];
             }
+            const auto out = planes(P.o_th, std::integral_constant<int, QS>{});
 #pragma unroll
             for (int i = 0; i < QS; ++i) {
               const CT cx = CT(LS::c[i][0]), cy = CT(LS::c[i][1]), cz = CT(LS::c[i][2]);
@@ -954,7 +974,7 @@ __global__ __launch_bounds__(Col3<CT>::NT, 1) void step3d_kernel(const DevParams
               const CT G = w * (cx * dHv[0] + cy * dHv[1] + cz * dHv[2]) * CT(1.0 / LS::cs2);
               CT gs = geq + (CT(1) - s1) * (cx * jf[0] + cy * jf[1] + cz * jf[2]) * CT(0.5) + (CT(1) - CT(0.5) * s1) * G;
               if (far_out(i)) gs = CT(2) * w * (K.theta0 - r_H) - gs;   // anti-bounce-back to theta0
-              st(P.o_th, i, gs);
+              st(out, i, gs);
             }
 #pragma unroll
             for (int a = 0; a < 3; ++a) hst(P.h_Hv + a, Hv[a]);
